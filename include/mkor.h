@@ -141,15 +141,23 @@ extern "C" {
                                   FP32 */
 #define MKOR_GEMM_FP32     1   /* fp32 MFMA (v_mfma_f32_32x32x2_f32), any d_in, d_out */
 #define MKOR_GEMM_SPLIT    2   /* 16-bit MFMA on a split of each fp32 operand into 16-bit
-                                  values.  fp32 times fp32: fp16 pairs, scaled per 32 rows
-                                  by a power of two, which hold a value x to 2^-23 |x| +
-                                  2^-39 (largest entry of those rows), three of the four
+                                  values, fp32 accumulation; each factor's diagonal apart,
+                                  in fp32.  fp32 times fp32: fp16 pairs, scaled per row of
+                                  the contraction by a power of two, which hold a value x
+                                  to 2^-23 |x| + 2^-39 (largest entry of its row, of a
+                                  factor the largest off its diagonal), three of the four
                                   partial products kept (the fourth below 2^-22 |x x'|).
                                   A bf16 G is one fp16 value per element, exact down to
-                                  2^-31 of the largest entry of the rows (or, transposed,
-                                  of the matrix) it is scaled with, and waits in the dW
-                                  buffer until the second GEMM writes dW.  Needs d_in and
-                                  d_out multiples of 64 (AUTO takes other sizes as well) */
+                                  2^-31 of the largest entry of its row (or, transposed,
+                                  of its column), and waits in the dW buffer until the
+                                  second GEMM writes dW.  A row or column of G far smaller
+                                  than the others keeps fp32's relative precision as long
+                                  as the factors couple it to larger ones no more strongly
+                                  than its size (as the SM updates do); a factor in which
+                                  rows of G many orders of magnitude (2^16 and more) below
+                                  the largest are strongly coupled among themselves needs
+                                  MKOR_GEMM_FP32 for those rows.  Needs d_in and d_out
+                                  multiples of 64 (AUTO takes other sizes as well) */
 
 /* largest supported d_in / d_out, and token rows of A / Gout */
 #define MKOR_MAX_DIM       32768

@@ -44,6 +44,18 @@ __device__ __forceinline__ uint4 gld_u4(const void* p) {
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// eight 16-bit values at any multiple of 2 bytes, four words at any of 4
+typedef unsigned int mk_u4w __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int mk_u4h __attribute__((ext_vector_type(4), aligned(2)));
+__device__ __forceinline__ uint4 gld_u4w(const void* p) {
+    const mk_u4w v = *(const MKOR_GLOBAL mk_u4w*)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint4 gld_u4h(const void* p) {
+    const mk_u4h v = *(const MKOR_GLOBAL mk_u4h*)p;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 __device__ __forceinline__ uint2 gld_u2(const void* p) {
     const mk_u2 v = *(const MKOR_GLOBAL mk_u2*)p;
     return make_uint2(v.x, v.y);
@@ -158,6 +170,35 @@ __device__ __forceinline__ float row_sums16(const float (&v)[16], int lane) {
     for (int k = 0; k < 2; ++k) c[k] = (h2 ? b[k + 2] : b[k]) + __shfl_xor(h2 ? b[k] : b[k + 2], 4, 64);
     float d = (h1 ? c[1] : c[0]) + __shfl_xor(h1 ? c[0] : c[1], 2, 64);
     return d + __shfl_xor(d, 1, 64);
+}
+
+// The same with the maximum in place of the sum.
+__device__ __forceinline__ float row_max16(const float (&v)[16], int lane) {
+    const bool h4 = (lane & 16) != 0, h3 = (lane & 8) != 0, h2 = (lane & 4) != 0, h1 = (lane & 2) != 0;
+    float a[8], b[4], c[2];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a[k] = fmaxf(h4 ? v[k + 8] : v[k], __shfl_xor(h4 ? v[k] : v[k + 8], 16, 64));
+#pragma unroll
+    for (int k = 0; k < 4; ++k) b[k] = fmaxf(h3 ? a[k + 4] : a[k], __shfl_xor(h3 ? a[k] : a[k + 4], 8, 64));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) c[k] = fmaxf(h2 ? b[k + 2] : b[k], __shfl_xor(h2 ? b[k] : b[k + 2], 4, 64));
+    const float d = fmaxf(h1 ? c[1] : c[0], __shfl_xor(h1 ? c[0] : c[1], 2, 64));
+    return fmaxf(d, __shfl_xor(d, 1, 64));
+}
+
+// The maxima over the wave of eight per-lane values: lanes 8 r .. 8 r + 7 end
+// with that of value r.
+__device__ __forceinline__ float row_max8(const float (&v)[8], int lane) {
+    const bool h5 = (lane & 32) != 0, h4 = (lane & 16) != 0, h3 = (lane & 8) != 0;
+    float a[4], b[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) a[k] = fmaxf(h5 ? v[k + 4] : v[k], __shfl_xor(h5 ? v[k] : v[k + 4], 32, 64));
+#pragma unroll
+    for (int k = 0; k < 2; ++k) b[k] = fmaxf(h4 ? a[k + 2] : a[k], __shfl_xor(h4 ? a[k] : a[k + 2], 16, 64));
+    float c = fmaxf(h3 ? b[1] : b[0], __shfl_xor(h3 ? b[0] : b[1], 8, 64));
+    c = fmaxf(c, __shfl_xor(c, 4, 64));
+    c = fmaxf(c, __shfl_xor(c, 2, 64));
+    return fmaxf(c, __shfl_xor(c, 1, 64));
 }
 
 }  // namespace mkor

@@ -549,9 +549,15 @@ int compute_layout(const mkor_layer* layers, int32_t n, Layout& Lo, bool spare) 
         if (needs_cvt(layers[i])) Lo.gh_off[i] = take(2 * (size_t)layers[i].d_in * layers[i].d_out);
     Lo.rq_off.assign(n, 0);
     for (int32_t i = 0; i < n; ++i)
-        if (is_split(layers[i]))   // (Q w) of the first GEMM's factor, one row per pending term, then G's block maxima
-            Lo.rq_off[i] = take(sizeof(float) * (2 * (size_t)tr_chunks(layers[i]) * stage_geom(layers[i], 1).cols +
-                                                 (is_swapped(layers[i]) ? (size_t)gpart_count(layers[i]) : 0)));
+        if (is_split(layers[i])) {   // (Q w) of the first GEMM's factor, one row per pending term, then G's column maxima
+            const size_t cols = stage_geom(layers[i], 1).cols;
+            Lo.rq_off[i] = take(sizeof(float) * cols * (2 * (size_t)tr_chunks(layers[i]) +
+                                                        (is_swapped(layers[i]) ? (size_t)gpart_count(layers[i]) : 0)));
+        }
+    Lo.mx_off.assign(n, 0);
+    for (int32_t i = 0; i < n; ++i)
+        if (is_split(layers[i]))
+            Lo.mx_off[i] = take(2 * sizeof(float) * ((size_t)layers[i].d_in + layers[i].d_out));
     Lo.rq2_off.assign(n, 0);
     for (int32_t i = 0; i < n; ++i)
         if (is_split(layers[i]) || is_half(layers[i])) {   // the second GEMM's (Q w) in parts (HgLayer.rq2)
@@ -669,6 +675,8 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
         R.mode = mode_d + i;
         if (!L.second_order) continue;
         const bool half = is_half(L);
+        // row maxima (split layers): Linv, Rinv, the first GEMM's Q, its output
+        float* mx = reinterpret_cast<float*>(base + lo.mx_off[i]);
         for (int side = 0; side < 2; ++side) {
             FactorDesc& f = fd[fi];
             f.P = side == 0 ? L.Linv : L.Rinv;
@@ -686,7 +694,7 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
             f.half = half ? 1 : 0;
             f.rank = layer_rank(L);
             f.lazy = lazy_factor(L, side) ? 1 : 0;
-            f.split = is_split(L) ? 1 : 0;
+            f.rmax = is_split(L) ? mx + (side == 0 ? 0 : L.d_in) : nullptr;
             f.mode = mode_d + i;
             for (int32_t r = 0; r < f.nblk; ++r) rb[bi++] = RowBlock{fi, r * rows};
             ++fi;
@@ -697,8 +705,7 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
         const int32_t ngp = (int32_t)gpart_count(L), ndp = (int32_t)dpart_count(L);
         R.gpart0 = gp; R.ngpart = ngp;
         R.dpart0 = dp; R.ndpart = ndp;
-        float* mxL = reinterpret_cast<float*>(base + lo.off_smpart + sizeof(float4) * fL.blk0);
-        float* mxR = reinterpret_cast<float*>(base + lo.off_smpart + sizeof(float4) * fR.blk0);
+        float *mxL = mx, *mxR = mx + L.d_in, *mxQ = mxR + L.d_out, *mxC = mxQ + (is_swapped(L) ? L.d_out : L.d_in);
         if (half) {
             // Y^T = R G^T (stored bf16 in the workspace), then dW_hat = L Y;
             // an fp32 G is first copied to bf16 in the workspace
@@ -761,7 +768,7 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
             A.part0 = gp; A.ntj = ceil_div(s1.cols, s1.bn);
             A.qf32 = 0; A.fq = 0; A.wide = s1.bm == SG_BI1H;
             A.rq = reinterpret_cast<float*>(base + lo.rq_off[i]);
-            A.pmax = mxL + SMP_W; A.qmax = mxR + SMP_Y; A.cmax = mxL + SMP_Z;
+            A.pmax = mxL; A.qmax = mxQ; A.cmax = mxC;
             A.mode = mode_d + i;
             for (int32_t r = 0; r < ngp; ++r) qdb[nqb++] = QdBlock{i, r, qd_rows_of(L)};
             HgLayer& B = s2l[i];
@@ -772,7 +779,7 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
             B.I = s2.rows; B.J = s2.cols; B.K = s2.K;
             B.part0 = dp; B.ntj = ceil_div(s2.cols, SG_BS);
             B.qf32 = 1; B.fq = 1;
-            B.pmax = mxL + SMP_Z; B.qmax = mxR + SMP_W; B.cmax = nullptr;
+            B.pmax = mxC; B.qmax = mxR; B.cmax = nullptr;
             B.mode = mode_d + i;
             gp += ngp;
             dp += ndp;
@@ -793,7 +800,7 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
             A.part0 = gp; A.ntj = ceil_div(s1.cols, s1.bn);
             A.qf32 = bf16 ? 0 : 1; A.fq = 0; A.wide = s1.bm == SG_BI1H;
             A.rq = reinterpret_cast<float*>(base + lo.rq_off[i]);
-            A.pmax = mxR + SMP_W; A.qmax = mxL + SMP_Y; A.cmax = mxR + SMP_Z;
+            A.pmax = mxR; A.qmax = mxQ; A.cmax = mxC;
             A.mode = mode_d + i;
             for (int32_t r = 0; r < ngp; ++r) qdb[nqb++] = QdBlock{i, r, qd_rows_of(L)};
             HgLayer& B = s2l[i];
@@ -804,7 +811,7 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
             B.I = s2.rows; B.J = s2.cols; B.K = s2.K;
             B.part0 = dp; B.ntj = ceil_div(s2.cols, SG_BS);
             B.qf32 = 1; B.fq = 0;
-            B.pmax = mxL + SMP_W; B.qmax = mxR + SMP_Z; B.cmax = nullptr;
+            B.pmax = mxL; B.qmax = mxC; B.cmax = nullptr;
             B.mode = mode_d + i;
             gp += ngp;
             dp += ndp;
@@ -874,11 +881,11 @@ int run_stage(const WsView& v, const mkor_params* prm, int32_t stage, hipStream_
             e = launch_sm_finalize(fd, lo.nfactors, smpart, gram, *prm, s);
             if (e != hipSuccess) return hip_fail(e, "sm_finalize launch");
             // rank-r updates are written into their factors at once
-            if (lo.nranked > 0) e = launch_sm_apply_rank(fd, rb, lo.nrowblocks, lo.nfactors, smpart, s);
+            if (lo.nranked > 0) e = launch_sm_apply_rank(fd, rb, lo.nrowblocks, lo.nfactors, s);
             if (e != hipSuccess) return hip_fail(e, "rank-r apply launch");
             return MKOR_OK;
         case MKOR_STAGE_GEMM_PREP: {
-            const SmaxArgs sx{fd, rb, lo.nrowblocks, smpart};
+            const SmaxArgs sx{fd, rb, lo.nrowblocks};
             e = launch_cvt_bf16(reinterpret_cast<const CvtItem*>(ws + lo.off_cvti),
                                 reinterpret_cast<const CvtBlock*>(ws + lo.off_cvtb), lo.ncvtblk, s);
             if (e != hipSuccess) return hip_fail(e, "bf16 gradient copy launch");

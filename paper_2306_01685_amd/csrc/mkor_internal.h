@@ -91,7 +91,7 @@ struct FactorDesc {
     int32_t           half;    // 1: S is stored in bf16 (d a multiple of 64)
     int32_t           rank;    // r vectors: x, u and w are d x r (vector l at + l * d)
     int32_t           lazy;    // rank 1, fp32: up to two pending terms (w holds 2 d floats)
-    int32_t           split;   // an operand of the split GEMMs, which need its block maxima
+    float*            rmax;    // workspace, d floats: row maxima for the split GEMMs (else null)
     const int32_t*    mode;    // the layer's mode word
 };
 
@@ -135,30 +135,26 @@ struct RowBlock {
     int32_t row0;
 };
 
-// Per row block of a factor, one float4 (the SM partials):
-//   x, y, z  the pass's {norm max, sum x_i u_i, sum x_i^2}, read by the finalize
-//            and free from then on until the next pass;
-//   w        the largest |S_ij| of the block's rows as they lie in the buffer,
-//            NaN passed over: left by the pass that last read or wrote S, or by
-//            the operand preparation where the factor has no pending term.
-// Row blocks of fp32 factors have 32 rows, the rows of an MFMA block, and the
-// split GEMMs scale their fp32 operands by 32-row blocks: w for a factor; y
-// for an fp32 G, whose rows j match those of the factor Linv; z for the
-// intermediate of the two GEMMs, whose rows match those of the first GEMM's
-// factor.
-constexpr int SMP_Y = 1, SMP_Z = 2, SMP_W = 3;
+// Per row block of a factor, one float4 (the SM partials): {norm max, sum x_i
+// u_i, sum x_i^2, unused}.
 
-// Row blocks per workgroup of the block maxima in the operand preparation.
+// Row maxima.  The split GEMMs scale each row of an fp32 operand by a power of
+// two taken from its largest entry: of a factor the largest |S_ij|, j != i, as
+// it lies in the buffer (FactorDesc.rmax: left by the pass that last read or
+// wrote S, or by the operand preparation where the factor has no pending term),
+// of G and of the intermediate of the two GEMMs the largest of all.  NaN are
+// passed over.
+
+// Row blocks per workgroup of the row maxima in the operand preparation.
 constexpr int SMAX_BLOCKS = 8;
 struct SmaxArgs {
     const FactorDesc* factors;
     const RowBlock*   blocks;
     int32_t           nblocks;   // 0: the pass of the same call left the maxima
-    float4*           smpart;
 };
 
-// The power of two by which a block whose largest entry is m is scaled before
-// it is split into fp16 pairs: m lands in [2^14, 2^15).  0 for a block of
+// The power of two by which a row whose largest entry is m is scaled before
+// it is split into fp16 pairs: m lands in [2^14, 2^15).  0 for a row of
 // zeros or with an infinity; at most 126, where every fp32 value is a multiple
 // of fp16's spacing.
 __device__ __forceinline__ int split_exp(float m) {
@@ -284,13 +280,13 @@ struct HgLayer {
     int32_t        fq;     // sgemm: the factor is the Q operand, C = P Q_eff^T (else C = P_eff Q^T)
     int32_t        wide;   // sgemm stage 1, one-plane Q: SG_BI1H x SG_BJ1H tiles (else SG_BI x SG_BJ)
     float*         rq;     // sgemm: (Q w) per Q row (FQ: (P w)), formed ahead of the GEMM
-    // sgemm: largest |entry| per 32 rows of P, of an fp32 Q and (stage 1) of C,
-    // every fourth float (a component of the SM partials)
+    // sgemm: row maxima of P, of Q and (stage 1) of C
     const float*   pmax;
     float*         qmax;
     float*         cmax;
     // sgemm stage 1, bf16 G: G itself (Q is the fp16 plane made of it), and,
-    // where Q is G^T, its block maxima (else null)
+    // where Q is G^T, its column maxima over ngmx ranges of rows, J floats each
+    // (else null)
     const void*    src;
     float*         gmx;
     int32_t        ngmx;
@@ -406,7 +402,7 @@ hipError_t launch_sm_pass(const FactorDesc* factors, const RowBlock* blocks, int
                           bool resident, hipStream_t stream);
 // writes the pending rank-r terms into the rank-r factors and clears them
 hipError_t launch_sm_apply_rank(const FactorDesc* factors, const RowBlock* blocks, int32_t nblocks,
-                                int32_t nfactors, float4* partials, hipStream_t stream);
+                                int32_t nfactors, hipStream_t stream);
 
 // One workgroup per factor: stabiliser decision and update coefficients from
 // the pass partials, new pending term (coefficients and w), stats.

@@ -20,16 +20,21 @@
 namespace mkor {
 namespace {
 
-// MKOR_NOALLOC_MAX_BYTES, and on top of it up to 256 bytes per layer, 32 per
-// 256 x 256 of its gradient and a float per 128 of its entries for descriptors
-// and partial sums, so that a list is not refused for the size of those
+// MKOR_NOALLOC_MAX_BYTES, and on top of it up to 1 KB per layer, 32 bytes per
+// 256 x 256 of its gradient, a float per 128 of its entries, two per row and
+// column and, bf16, one per 32 of its entries for descriptors, partial sums and
+// row maxima, so that a list is not refused for the size of those
 constexpr size_t DESC_MAX = 8u << 20;
 size_t room(const mkor_layer* layers, int32_t n) {
     size_t b = 0;
     for (int32_t i = 0; i < n; ++i)
         b += 256 + 32 * ((size_t)(layers[i].d_in + 255) / 256) * ((size_t)(layers[i].d_out + 255) / 256) +
              4 * (size_t)std::max(layers[i].d_in, layers[i].d_out) *
-                 (((size_t)std::min(layers[i].d_in, layers[i].d_out) + 255) / 128) + 512;
+                 (((size_t)std::min(layers[i].d_in, layers[i].d_out) + 255) / 128) + 512 +
+             8 * ((size_t)layers[i].d_in + layers[i].d_out) + 256 +
+             (layers[i].grad_dtype == MKOR_DTYPE_BF16 && layers[i].d_in > layers[i].d_out
+                  ? 4 * (size_t)layers[i].d_out * ((layers[i].d_out + 31) / 32)
+                  : 0);
     return (size_t)MKOR_NOALLOC_MAX_BYTES + std::min(DESC_MAX, b);
 }
 static __device__ __align__(256) unsigned char scratch[MKOR_NOALLOC_MAX_BYTES + DESC_MAX];

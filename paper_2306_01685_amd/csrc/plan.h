@@ -65,7 +65,8 @@ struct Layout {
     std::vector<size_t> u_off, w_off, x_off;   // per factor / per layer offsets (bytes)
     std::vector<size_t> gh_off;                // per layer: bf16 copy of an fp32 G (bf16 factors)
     std::vector<size_t> rq2_off;               // per layer: stage-2 (Q w) of split and bf16-factor layers
-    std::vector<size_t> rq_off;                // per layer: stage-1 (Q w) of split layers, G's block maxima
+    std::vector<size_t> rq_off;                // per layer: stage-1 (Q w) of split layers, G's column maxima
+    std::vector<size_t> mx_off;                // per layer: row maxima of split layers (Linv, Rinv, Q, C of stage 1)
 };
 
 int check_params(const mkor_params* p);

@@ -51,12 +51,6 @@ __device__ __forceinline__ float wave_nanmax(float v) {
     return v;
 }
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-
 __device__ __forceinline__ float absacc(float acc, float v, int maxabs) {
     return maxabs ? nanmax(acc, fabsf(v)) : acc + fabsf(v);
 }
@@ -76,15 +70,30 @@ __device__ __forceinline__ float apply_b(const Pending& q, float v, float wi, fl
 // Columns 0 .. d / 4 * 4 - 1 of rows rbase .. rbase + nr - 1 of one fp32 factor.
 // FULL: nr = R.
 // ST: write the current values into S; T2: the pending term has two parts.
-// smx: the largest |S_ij| as the buffer holds it afterwards (NaN passed over).
+// smx: per row, the largest |S_ij|, j != i, as the buffer holds it afterwards
+// (NaN passed over).
 __device__ __forceinline__ float absmax4(float m, const float4& v) {
     m = fmaxf(fmaxf(m, fabsf(v.x)), fabsf(v.y));
     return fmaxf(fmaxf(m, fabsf(v.z)), fabsf(v.w));
 }
 
+// v with a zero in place of component c (known at compile time) where `diag`
+__device__ __forceinline__ float4 off_diag(float4 v, int c, bool diag) {
+    float& x = c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w;
+    x = diag ? 0.f : x;
+    return v;
+}
+
+// The rows' maxima, per-lane values of a wave's 8 rows, into the factor's table.
+__device__ __forceinline__ void put_row_max(const FactorDesc& f, int rbase, int nr, int lane, const float (&smx)[8]) {
+    if (f.rmax == nullptr) return;   // uniform
+    const float m = row_max8(smx, lane);
+    if ((lane & 7) == 0 && (lane >> 3) < nr) gst(f.rmax + rbase + (lane >> 3), m);
+}
+
 template <int RW, bool NT, bool HAS, bool MV, bool FULL, bool ST = HAS, bool T2 = false>
 __device__ __forceinline__ void pass_rows4(const FactorDesc& f, const Pending& q, int rbase, int nr,
-                                           int lane, int maxabs, float (&dot)[RW], float (&nrm)[RW], float& smx) {
+                                           int lane, int maxabs, float (&dot)[RW], float (&nrm)[RW], float (&smx)[RW]) {
     const int d = f.d, d4 = d >> 2;
     float* __restrict__ P = static_cast<float*>(f.P) + (size_t)rbase * d;
     float wi[RW], wi2[RW];
@@ -94,7 +103,9 @@ __device__ __forceinline__ void pass_rows4(const FactorDesc& f, const Pending& q
         wi2[r] = (T2 && (FULL || r < nr)) ? gld(f.w + d + rbase + r) : 0.f;
     }
 
+    static_assert(RW % 4 == 0, "rbase is a multiple of RW: row r's diagonal is component r & 3");
     for (int j = lane; j < d4; j += 64) {
+        const int jd = j - (rbase >> 2);   // r >> 2 where this lane holds row r's diagonal
         float4 p[RW];
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
@@ -108,7 +119,7 @@ __device__ __forceinline__ void pass_rows4(const FactorDesc& f, const Pending& q
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
             if (!FULL && r >= nr) break;
-            if constexpr (MV && !(HAS && ST)) smx = absmax4(smx, p[r]);
+            if constexpr (MV && !(HAS && ST)) smx[r] = absmax4(smx[r], off_diag(p[r], r & 3, jd == r >> 2));
             if constexpr (HAS) {
                 p[r].x = apply(q, p[r].x, wi[r], wv.x);
                 p[r].y = apply(q, p[r].y, wi[r], wv.y);
@@ -140,7 +151,7 @@ __device__ __forceinline__ void pass_rows4(const FactorDesc& f, const Pending& q
                     else              gst4u(P + (size_t)r * d + 4 * j, p[r]);
                 }
             }
-            if constexpr (MV && HAS && ST) smx = absmax4(smx, p[r]);
+            if constexpr (MV && HAS && ST) smx[r] = absmax4(smx[r], off_diag(p[r], r & 3, jd == r >> 2));
             if constexpr (MV) {
                 dot[r] = fmaf(p[r].x, xv.x, dot[r]);
                 dot[r] = fmaf(p[r].y, xv.y, dot[r]);
@@ -232,7 +243,7 @@ __device__ __forceinline__ void pass_rows8h(const FactorDesc& f, const Pending& 
 // The last d % 4 columns (scalar accesses).
 template <int RW, bool HAS, bool MV>
 __device__ __forceinline__ void pass_rows1(const FactorDesc& f, const Pending& q, int rbase, int nr,
-                                           int lane, int maxabs, float (&dot)[RW], float (&nrm)[RW], float& smx) {
+                                           int lane, int maxabs, float (&dot)[RW], float (&nrm)[RW], float (&smx)[RW]) {
     const int d = f.d;
     float* __restrict__ P = static_cast<float*>(f.P) + (size_t)rbase * d;
     float wi[RW];
@@ -254,7 +265,7 @@ __device__ __forceinline__ void pass_rows1(const FactorDesc& f, const Pending& q
             if constexpr (MV) {
                 dot[r] = fmaf(p, xv, dot[r]);
                 nrm[r] = absacc(nrm[r], p, maxabs);
-                smx = fmaxf(smx, fabsf(p));
+                smx[r] = fmaxf(smx[r], rbase + r == j ? 0.f : fabsf(p));
             }
         }
     }
@@ -265,7 +276,7 @@ __device__ __forceinline__ void pass_rows1(const FactorDesc& f, const Pending& q
 // lazy: fp32 with d a multiple of 64.
 template <int RW, bool HALF, bool NT, bool HAS, bool MV, bool ST = HAS, bool T2 = false>
 __device__ __forceinline__ void pass_rows(const FactorDesc& f, const Pending& q, int rbase, int nr,
-                                          int lane, int maxabs, float (&dot)[RW], float (&nrm)[RW], float& smx) {
+                                          int lane, int maxabs, float (&dot)[RW], float (&nrm)[RW], float (&smx)[RW]) {
     if constexpr (T2 || ST != HAS) {
         if constexpr (!HALF) {
             if (nr == RW) pass_rows4<RW, NT, HAS, MV, true, ST, T2>(f, q, rbase, nr, lane, maxabs, dot, nrm, smx);
@@ -298,9 +309,9 @@ __device__ __forceinline__ void pass_block(const FactorDesc& f, const RowBlock& 
     const int rbase = rb.row0 + wave * RW;
     const int nr = max(0, min(RW, f.d - rbase));
 
-    float dot[RW], nrm[RW], smx = 0.f;
+    float dot[RW], nrm[RW], smx[RW];
 #pragma unroll
-    for (int r = 0; r < RW; ++r) { dot[r] = 0.f; nrm[r] = 0.f; }
+    for (int r = 0; r < RW; ++r) dot[r] = nrm[r] = smx[r] = 0.f;
     // a lazy factor with one pending term is only read: the next term joins
     // it (finalize), and the pass of the step after writes both
     const bool two = q.has == 2, store = has && (!matvec || !f.lazy || two);
@@ -322,7 +333,7 @@ __device__ __forceinline__ void pass_block(const FactorDesc& f, const RowBlock& 
         dot[r] = wave_sum(dot[r]);
         nrm[r] = maxabs ? wave_nanmax(nrm[r]) : wave_sum(nrm[r]);
     }
-    smx = wave_max(smx);
+    if constexpr (!HALF) put_row_max(f, rbase, nr, lane, smx);
 
     if (lane == 0) {
         float mx = 0.f, sxu = 0.f, sxx = 0.f;
@@ -336,7 +347,7 @@ __device__ __forceinline__ void pass_block(const FactorDesc& f, const RowBlock& 
             sxu = fmaf(xr, dot[r], sxu);
             sxx = fmaf(xr, xr, sxx);
         }
-        sred[wave] = make_float4(mx, sxu, sxx, smx);
+        sred[wave] = make_float4(mx, sxu, sxx, 0.f);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -345,7 +356,6 @@ __device__ __forceinline__ void pass_block(const FactorDesc& f, const RowBlock& 
             acc.x = nanmax(acc.x, sred[w].x);
             acc.y += sred[w].y;
             acc.z += sred[w].z;
-            acc.w = fmaxf(acc.w, sred[w].w);
         }
         gst4(reinterpret_cast<float*>(partials + b), acc);
     }
@@ -385,7 +395,7 @@ constexpr int RR = SM_ROWS_PER_WAVE;
 
 template <bool HAS, bool MV, bool VEC>
 __device__ __forceinline__ void rank_rows(const FactorDesc& f, const Pending& q, int rbase, int nr, int lane,
-                                          int maxabs, float (&dot)[RR][MAXR], float (&nrm)[RR], float& smx) {
+                                          int maxabs, float (&dot)[RR][MAXR], float (&nrm)[RR], float (&smx)[RR]) {
     const int d = f.d, rk = f.rank;
     float* __restrict__ P = static_cast<float*>(f.P) + (size_t)rbase * d;
     float swi[RR][MAXR];
@@ -408,6 +418,7 @@ __device__ __forceinline__ void rank_rows(const FactorDesc& f, const Pending& q,
     if constexpr (VEC) {
         const int d4 = d >> 2;
         for (int j = lane; j < d4; j += 64) {
+            const int jd = j - (rbase >> 2);   // r >> 2 where this lane holds row r's diagonal
             float4 p[RR];
 #pragma unroll
             for (int r = 0; r < RR; ++r)
@@ -434,7 +445,7 @@ __device__ __forceinline__ void rank_rows(const FactorDesc& f, const Pending& q,
 #pragma unroll
                 for (int c = 0; c < 4; ++c) v[c] = elem(r, 4 * j + c, v[c], wj[c]);
                 if constexpr (HAS) gst4u(P + (size_t)r * d + 4 * j, make_float4(v[0], v[1], v[2], v[3]));
-                smx = absmax4(smx, make_float4(v[0], v[1], v[2], v[3]));
+                if constexpr (!MV) smx[r] = absmax4(smx[r], off_diag(make_float4(v[0], v[1], v[2], v[3]), r & 3, jd == r >> 2));
                 if constexpr (MV) {
 #pragma unroll
                     for (int l = 0; l < MAXR; ++l) {
@@ -463,7 +474,7 @@ __device__ __forceinline__ void rank_rows(const FactorDesc& f, const Pending& q,
                 if (r >= nr) break;
                 float v = elem(r, j, gld(P + (size_t)r * d + j), wj);
                 if constexpr (HAS) gst(P + (size_t)r * d + j, v);
-                smx = fmaxf(smx, fabsf(v));
+                if constexpr (!MV) smx[r] = fmaxf(smx[r], rbase + r == j ? 0.f : fabsf(v));
                 if constexpr (MV) {
 #pragma unroll
                     for (int l = 0; l < MAXR; ++l)
@@ -483,9 +494,9 @@ __device__ __forceinline__ void rank_rows(const FactorDesc& f, const Pending& q,
 // read pass meets no pending term; should it meet one, the scalar path applies
 // and writes it before the products.
 template <int MV>
-__global__ __launch_bounds__(SM_THREADS) void sm_pass_rank_kernel(
+__global__ __launch_bounds__(SM_THREADS, MV ? 3 : 4) void sm_pass_rank_kernel(
     const FactorDesc* __restrict__ factors, const RowBlock* __restrict__ blocks,
-    float4* __restrict__ partials, float* __restrict__ gram, int nblocks, int maxabs) {
+    float4* __restrict__ partials, float* __restrict__ gram, int nblocks, int maxabs, int step) {
     constexpr bool matvec = MV != 0;
     __shared__ float4 sred[SM_THREADS / 64];
     __shared__ float sgram[SM_THREADS / 64][GRAM];
@@ -497,14 +508,17 @@ __global__ __launch_bounds__(SM_THREADS) void sm_pass_rank_kernel(
         if (matvec && !gld_i32(f.mode)) continue;   // first-order layer this step
         const Pending q = *f.pend;
         const bool has = q.has != 0;
-        if (!has && !matvec) continue;
+        // a factor without a term is left alone, but in a step, where the update
+        // may have left it unchanged (a value that was not finite), its row
+        // maxima are taken
+        if (!has && !matvec && (!step || f.rmax == nullptr || !gld_i32(f.mode))) continue;
         const int rbase = rb.row0 + wave * RR;
         const int nr = max(0, min(RR, f.d - rbase));
         const int rk = f.rank;
-        float dot[RR][MAXR], nrm[RR], smx = 0.f;
+        float dot[RR][MAXR], nrm[RR], smx[RR];
 #pragma unroll
         for (int r = 0; r < RR; ++r) {
-            nrm[r] = 0.f;
+            nrm[r] = smx[r] = 0.f;
 #pragma unroll
             for (int l = 0; l < MAXR; ++l) dot[r][l] = 0.f;
         }
@@ -520,22 +534,12 @@ __global__ __launch_bounds__(SM_THREADS) void sm_pass_rank_kernel(
                 if (has) rank_rows<true, true, false>(f, q, rbase, nr, lane, maxabs, dot, nrm, smx);
                 else     rank_rows<false, true, true>(f, q, rbase, nr, lane, maxabs, dot, nrm, smx);
             } else {
-                rank_rows<true, false, true>(f, q, rbase, nr, lane, maxabs, dot, nrm, smx);
+                if (has) rank_rows<true, false, true>(f, q, rbase, nr, lane, maxabs, dot, nrm, smx);
+                else     rank_rows<false, false, true>(f, q, rbase, nr, lane, maxabs, dot, nrm, smx);
             }
         }
-        // block maxima of the buffer (see SMP_W); a write-back outside a step
-        // (no partials) leaves them to the next pass or preparation
-        smx = wave_max(smx);
-        if (!matvec) {
-            if (partials == nullptr) continue;   // uniform
-            if (lane == 0) sred[wave].w = smx;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                float m = sred[0].w;
-                for (int w = 1; w < SM_THREADS / 64; ++w) m = fmaxf(m, sred[w].w);
-                gst(reinterpret_cast<float*>(partials + b) + SMP_W, m);
-            }
-            __syncthreads();   // sred is reused by the next row block
+        if constexpr (!matvec) {
+            put_row_max(f, rbase, nr, lane, smx);   // of the buffer as it is now
             continue;
         }
 #pragma unroll
@@ -575,16 +579,13 @@ __global__ __launch_bounds__(SM_THREADS) void sm_pass_rank_kernel(
 #pragma unroll
             for (int r = 0; r < RR; ++r)
                 if (r < nr) mx = nanmax(mx, nrm[r]);
-            sred[wave] = make_float4(mx, 0.f, 0.f, smx);
+            sred[wave] = make_float4(mx, 0.f, 0.f, 0.f);
         }
         static_assert(RR * MAXR <= 64 && GRAM == 2 * MAXR * MAXR && GRAM <= 64, "one lane per x value and Gram entry");
         __syncthreads();
         if (threadIdx.x == 0) {
             float4 acc = sred[0];
-            for (int w = 1; w < SM_THREADS / 64; ++w) {
-                acc.x = nanmax(acc.x, sred[w].x);
-                acc.w = fmaxf(acc.w, sred[w].w);
-            }
+            for (int w = 1; w < SM_THREADS / 64; ++w) acc.x = nanmax(acc.x, sred[w].x);
             gst4(reinterpret_cast<float*>(partials + b), acc);
         }
         if (threadIdx.x < GRAM) {
@@ -827,19 +828,19 @@ hipError_t launch_sm_pass(const FactorDesc* factors, const RowBlock* blocks, int
     if (e != hipSuccess || !ranked) return e;
     if (matvec)
         hipLaunchKernelGGL(sm_pass_rank_kernel<1>, dim3(grid), dim3(SM_THREADS), 0, stream, factors, blocks,
-                           partials, gram, nblocks, maxabs);
+                           partials, gram, nblocks, maxabs, 1);
     else
         hipLaunchKernelGGL(sm_pass_rank_kernel<0>, dim3(grid), dim3(SM_THREADS), 0, stream, factors, blocks,
-                           (float4*)nullptr, gram, nblocks, maxabs);
+                           partials, gram, nblocks, maxabs, 0);
     return hipGetLastError();
 }
 
 hipError_t launch_sm_apply_rank(const FactorDesc* factors, const RowBlock* blocks, int32_t nblocks,
-                                int32_t nfactors, float4* partials, hipStream_t stream) {
+                                int32_t nfactors, hipStream_t stream) {
     if (nblocks <= 0 || nfactors <= 0) return hipSuccess;
     const int32_t grid = (SM_GRID > 0 && nblocks > SM_GRID) ? SM_GRID : nblocks;
     hipLaunchKernelGGL(sm_pass_rank_kernel<0>, dim3(grid), dim3(SM_THREADS), 0, stream, factors, blocks,
-                       partials, (float*)nullptr, nblocks, 0);
+                       (float4*)nullptr, (float*)nullptr, nblocks, 0, 1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(sm_reset_kernel, dim3((nfactors + 255) / 256), dim3(256), 0, stream, factors,
