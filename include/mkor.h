@@ -124,9 +124,9 @@ extern "C" {
                                      step); u_raw = P x, norm and s partials */
 #define MKOR_STAGE_SM_FINALIZE 2  /* stabiliser decision, new pending rank-1 term */
 #define MKOR_STAGE_GEMM_PREP  3   /* operands of the 16-bit MFMA paths: bf16 copy of an fp32 G
-                                     (bf16 factors); split path: fp16 copy of a bf16 G (G^T
-                                     where d_in > d_out), scales, (Q w) and ||G||^2 partials
-                                     of its first GEMM */
+                                     (bf16 factors); split path: fp16 copy of a bf16 G (in the
+                                     dW buffer; G^T where d_in > d_out), scales, (Q w) and
+                                     ||G||^2 partials of its first GEMM */
 #define MKOR_STAGE_GEMM_XT    4   /* first GEMM: X^T = (Linv G)^T (fp32 MFMA), Y^T = Rinv G^T
                                      (bf16 MFMA paths) or X = Linv G (split path, bf16 G,
                                      d_in > d_out), ||G||^2 partials (the other paths) */
@@ -149,16 +149,15 @@ extern "C" {
                                   partial products kept (the fourth below 2^-22 |x x'|).
                                   A bf16 G is one fp16 value per element, exact down to
                                   2^-31 of the largest entry of its row (or, transposed,
-                                  of its column), in the workspace (mkor_step_noalloc: in
-                                  the dW buffer until the second GEMM writes dW).
-                                  A row or column of G far smaller than the others keeps
-                                  fp32's relative precision as long as the factors couple
-                                  it to larger ones no more strongly than its size (as the
-                                  SM updates do); a factor in which rows of G many orders
-                                  of magnitude (2^16 and more) below the largest are
-                                  strongly coupled among themselves needs MKOR_GEMM_FP32
-                                  for those rows.  Needs d_in and d_out multiples of 64
-                                  (AUTO takes other sizes as well) */
+                                  of its column), and waits in the dW buffer until the
+                                  second GEMM writes dW.  A row or column of G far smaller
+                                  than the others keeps fp32's relative precision as long
+                                  as the factors couple it to larger ones no more strongly
+                                  than its size (as the SM updates do); a factor in which
+                                  rows of G many orders of magnitude (2^16 and more) below
+                                  the largest are strongly coupled among themselves needs
+                                  MKOR_GEMM_FP32 for those rows.  Needs d_in and d_out
+                                  multiples of 64 (AUTO takes other sizes as well) */
 
 /* largest supported d_in / d_out, and token rows of A / Gout */
 #define MKOR_MAX_DIM       32768
@@ -208,7 +207,8 @@ typedef struct mkor_layer {
     float*       g;             /* d_out x rank, mean output gradient(s), vector l at g + l * d_out
                                    (a and g unused if second_order = 0) */
     const void*  G;             /* d_in x d_out gradient, grad_dtype elements */
-    float*       dW;            /* d_in x d_out fp32 output */
+    float*       dW;            /* d_in x d_out fp32 output; scratch of a preconditioning until
+                                   it has run */
     void*        stats;         /* optional device mkor_layer_stats*, may be NULL */
     /* Rank-1 approximation from token rows (Algorithm 1, its first two lines).
      * rows = 0: the caller supplies a and g.  rows > 0 (second-order layers

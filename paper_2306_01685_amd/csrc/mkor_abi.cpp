@@ -416,7 +416,7 @@ TilePlan tiles_of(const Layout& lo, int stage, int family) { return TilePlan{lo.
 
 }  // namespace
 
-int compute_layout(const mkor_layer* layers, int32_t n, Layout& Lo, bool planes, bool spare) {
+int compute_layout(const mkor_layer* layers, int32_t n, Layout& Lo, bool spare) {
     for (int fam = 0; fam < 3; ++fam)
         for (int stage = 1; stage <= 2; ++stage) {
             // (fp32 MFMA tiles, the layers with a side below 64, keep whole
@@ -553,12 +553,6 @@ int compute_layout(const mkor_layer* layers, int32_t n, Layout& Lo, bool planes,
             const size_t cols = stage_geom(layers[i], 1).cols;
             Lo.rq_off[i] = take(sizeof(float) * cols * (2 * (size_t)tr_chunks(layers[i]) +
                                                         (is_swapped(layers[i]) ? (size_t)gpart_count(layers[i]) : 0)));
-        }
-    Lo.gp_off.assign(n, 0);
-    for (int32_t i = 0; i < n; ++i)
-        if (planes && is_split(layers[i]) && layers[i].grad_dtype == MKOR_DTYPE_BF16) {
-            const StageGeom g = stage_geom(layers[i], 1);
-            Lo.gp_off[i] = take(2 * (size_t)g.cols * align_up(g.K, 64));
         }
     Lo.mx_off.assign(n, 0);
     for (int32_t i = 0; i < n; ++i)
@@ -757,17 +751,16 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
             dp += ndp;
             continue;
         }
-        // a bf16 G's fp16 plane, made by the operand preparation
-        const void* plane = lo.gp_off[i] ? static_cast<const void*>(base + lo.gp_off[i]) : L.dW;
         if (is_swapped(L)) {
-            // X = L G with Q = G^T (fp16), then dW_hat = X R with the factor R as
+            // X = L G with Q = G^T (fp16, which waits in the dW buffer until the
+            // second GEMM writes it), then dW_hat = X R with the factor R as
             // the Q operand
             void* X = base + lo.x_off[i];
             for (int32_t h = 0; h < tr_chunks(L); ++h)
                 for (int32_t c0 = 0; c0 < L.d_out; c0 += 64) trb[ntb++] = TrBlock{i, h, c0, 0};
             const StageGeom s1 = stage_geom(L, 1, lo.small), s2 = stage_geom(L, 2, lo.small);
             HgLayer& A = s1l[i];
-            A.P = L.Linv; A.Q = plane; A.C = X;
+            A.P = L.Linv; A.Q = L.dW; A.C = X;
             A.src = L.G; A.nrq = tr_chunks(L);
             A.gmx = reinterpret_cast<float*>(base + lo.rq_off[i]) + 2 * (size_t)A.nrq * s1.cols; A.ngmx = ngp;
             A.pend = fL.pend; A.w = fL.w;
@@ -798,7 +791,9 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
             void* Yt = base + lo.x_off[i];
             const StageGeom s1 = stage_geom(L, 1, lo.small), s2 = stage_geom(L, 2, lo.small);
             HgLayer& A = s1l[i];
-            A.P = L.Rinv; A.Q = bf16 ? plane : L.G; A.C = Yt;
+            // (bf16 G: its fp16 plane waits in the dW buffer until the second
+            // GEMM writes it)
+            A.P = L.Rinv; A.Q = bf16 ? L.dW : L.G; A.C = Yt;
             A.src = L.G; A.nrq = 1;
             A.pend = fR.pend; A.w = fR.w;
             A.I = s1.rows; A.J = s1.cols; A.K = s1.K;

@@ -107,7 +107,7 @@ extern "C" int mkor_step_noalloc(const mkor_layer* layers, int32_t n, const mkor
     int st = check_layers(layers, n, nullptr, 0);
     if (st != MKOR_OK) return st;
     Layout lo;
-    st = compute_layout(layers, n, lo, false);
+    st = compute_layout(layers, n, lo);
     if (st != MKOR_OK) return st;
     st = check_run_params(params, lo.nranked);
     if (st != MKOR_OK) return st;
@@ -122,7 +122,7 @@ extern "C" int mkor_step_noalloc(const mkor_layer* layers, int32_t n, const mkor
                 L.gemm_path = MKOR_GEMM_FP32;
         layers = lean.data();
         lo = Layout();
-        st = compute_layout(layers, n, lo, false, true);
+        st = compute_layout(layers, n, lo, true);
         if (st != MKOR_OK) return st;
     }
     if (lo.total > most)

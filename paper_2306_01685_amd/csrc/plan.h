@@ -66,7 +66,6 @@ struct Layout {
     std::vector<size_t> gh_off;                // per layer: bf16 copy of an fp32 G (bf16 factors)
     std::vector<size_t> rq2_off;               // per layer: stage-2 (Q w) of split and bf16-factor layers
     std::vector<size_t> rq_off;                // per layer: stage-1 (Q w) of split layers, G's column maxima
-    std::vector<size_t> gp_off;                // per layer: fp16 plane of a bf16 G (split layers; 0: in the dW buffer)
     std::vector<size_t> mx_off;                // per layer: row maxima of split layers (Linv, Rinv, Q, C of stage 1)
 };
 
@@ -76,10 +75,8 @@ int check_run_params(const mkor_params* params, int32_t nranked);
 // Sizes, pointers, alignment, and overlaps among the buffers of the layers
 // and the workspace [ws, ws + ws_bytes) (ws may be NULL).
 int check_layers(const mkor_layer* layers, int32_t n, const void* ws, size_t ws_bytes);
-// planes: the fp16 planes of bf16 gradients have workspace (else they lie in the
-// dW buffers until the second GEMM writes dW)
 // spare: the fewest table and partial bytes (large tiles only)
-int compute_layout(const mkor_layer* layers, int32_t n, Layout& lo, bool planes = true, bool spare = false);
+int compute_layout(const mkor_layer* layers, int32_t n, Layout& lo, bool spare = false);
 // The descriptor tables of a workspace that starts at device address `base`:
 // host.size() == lo.table_bytes, to be copied to [base, base + table_bytes).
 // Every pending term starts empty.
