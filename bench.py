@@ -536,7 +536,6 @@ def measure(w, args, factor_dtype, gemm_path="auto", sample_power=False):
             # the clock the dominant GEMM runs at: at the board's power limit it
             # is below the nominal clock its peak assumes
             stage = [1, 2, 4, 5, 6][dom]
-            plan.run_stage(params, 3)   # the first GEMM's operand: the second one's output replaces it
             pw = clock_during(lambda: plan.run_stage(params, stage), args.power_seconds)
             if pw is not None:
                 peak_clk = roof["peak"] * pw["gfx_mhz"] / NOMINAL_GFX_MHZ
@@ -755,7 +754,6 @@ def power_profile(args):
     for fdt, path, tag in runs:
         layers, plan, p = make(fdt, path)
         phase(f"{tag}: step", lambda: plan.step(p))
-        plan.run_stage(p, stage["gemm_prep"])   # the step's second GEMM replaced the first one's operand
         phase(f"{tag}: first GEMM", lambda: plan.run_stage(p, stage["gemm_xt"]))
         phase(f"{tag}: second GEMM", lambda: plan.run_stage(p, stage["gemm_dw"]))
         if tag == "split":

@@ -308,7 +308,9 @@ int mkor_step(mkor_plan* plan, const mkor_params* params, void* stream);
 /* Launches one kernel of a step (MKOR_STAGE_*), for profiling and per-kernel
  * timing.  Launching stages 0..MKOR_NUM_STAGES-1 in order on one stream is
  * exactly mkor_step; a stage launched out of that order reads whatever the
- * workspace holds from earlier launches. */
+ * workspace holds from earlier launches.  (The split's copy of a bf16 G lies in
+ * the dW buffer: MKOR_STAGE_GEMM_XT after a second GEMM launches the preparation
+ * again ahead of the first one.) */
 int mkor_run_stage(mkor_plan* plan, const mkor_params* params, int32_t stage, void* stream);
 
 /* Writes the current value of every inverse factor (buffer + pending term)

@@ -979,6 +979,8 @@ struct mkor_plan {
     std::vector<uint8_t> rank1;    // per layer: second-order with a rank-1 update (leaves pending terms)
     std::vector<int32_t> mode;     // per layer: the mode word as the calls on the plan set it
     int32_t pending = 0;           // a factor update ran since creation or the last sync
+    bool planes = false;           // a split layer has a bf16 G, whose fp16 plane lies in the dW buffer
+    bool spent = true;             // the second GEMM has written over those since their preparation
 };
 
 extern "C" {
@@ -1055,6 +1057,7 @@ int mkor_plan_create(const mkor_layer* layers, int32_t n, void* d_workspace, siz
         plan->planned[i] = (uint8_t)L.second_order;
         plan->rank1[i] = (uint8_t)(L.second_order == 1 && L.rank <= 1);
         plan->mode[i] = L.second_order;
+        plan->planes |= is_split(L) && L.grad_dtype == MKOR_DTYPE_BF16;
     }
     if (lo.table_bytes > 0) {
         hipError_t e = hipMemcpy(base, host.data(), lo.table_bytes, hipMemcpyHostToDevice);
@@ -1073,9 +1076,12 @@ static int check_plan_params(const mkor_plan* plan, const mkor_params* params) {
     return check_run_params(params, plan->lo.nranked);
 }
 
-// A range that includes the factor update leaves pending terms on the
-// rank-1 factors of the layers whose mode is second-order.
-static void note_update(mkor_plan* p, int32_t first, int32_t last) {
+// What a range of stages leaves behind: a factor update, pending terms on the
+// rank-1 factors of the layers whose mode is second-order; the operand
+// preparation, its planes; the second GEMM, none of them.
+static void note_stages(mkor_plan* p, int32_t first, int32_t last) {
+    if (first <= MKOR_STAGE_GEMM_PREP && last >= MKOR_STAGE_GEMM_PREP) p->spent = false;
+    if (first <= MKOR_STAGE_GEMM_DW && last >= MKOR_STAGE_GEMM_DW) p->spent = true;
     if (first > MKOR_STAGE_SM_FINALIZE || last < MKOR_STAGE_SM_FINALIZE) return;
     for (int32_t i = 0; i < p->n; ++i)
         if (p->rank1[i] && p->mode[i]) p->pending = 1;
@@ -1083,7 +1089,7 @@ static void note_update(mkor_plan* p, int32_t first, int32_t last) {
 
 static int run_range(mkor_plan* p, const mkor_params* prm, int32_t first, int32_t last, hipStream_t s) {
     const int st = run_range(view(p), prm, first, last, s);
-    if (st == MKOR_OK) note_update(p, first, last);
+    if (st == MKOR_OK) note_stages(p, first, last);
     return st;
 }
 
@@ -1216,8 +1222,13 @@ int mkor_run_stage(mkor_plan* plan, const mkor_params* params, int32_t stage, vo
         "mkor_run_stage: means", "mkor_run_stage: sm_pass", "mkor_run_stage: sm_finalize", "mkor_run_stage: gemm_prep",
         "mkor_run_stage: gemm_xt", "mkor_run_stage: gemm_dw", "mkor_run_stage: rescale"};
     const TraceRange range(names[stage]);
+    if (stage == MKOR_STAGE_GEMM_XT && plan->planes && plan->spent) {   // its operand is gone: made again
+        st = run_stage(view(plan), params, MKOR_STAGE_GEMM_PREP, static_cast<hipStream_t>(stream));
+        if (st != MKOR_OK) return st;
+        note_stages(plan, MKOR_STAGE_GEMM_PREP, MKOR_STAGE_GEMM_PREP);
+    }
     st = run_stage(view(plan), params, stage, static_cast<hipStream_t>(stream));
-    if (st == MKOR_OK) note_update(plan, stage, stage);
+    if (st == MKOR_OK) note_stages(plan, stage, stage);
     return st;
 }
 
