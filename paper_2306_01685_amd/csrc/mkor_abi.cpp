@@ -9,7 +9,6 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <map>
 #include <new>
 #include <string>
 #include <vector>
@@ -253,6 +252,7 @@ struct SuperTile { int32_t layer, tm0, tn0, nm, nn, K; };
 typedef std::vector<std::vector<SuperTile>> SuperQueues;
 SuperQueues super_queues(const mkor_layer* layers, int32_t n, int stage, int family, TilePlan tp) {
     std::vector<SuperTile> sup;
+    sup.reserve(64);
     for (int32_t i = 0; i < n; ++i) {
         const mkor_layer& L = layers[i];
         if (!L.second_order || gemm_family(L) != family) continue;
@@ -264,14 +264,16 @@ SuperQueues super_queues(const mkor_layer* layers, int32_t n, int stage, int fam
                 sup.push_back(SuperTile{i, a, b, std::min(sm, tm - a), std::min(sn, tn - b), g.K});
     }
     if (sup.empty()) return {};
-    std::stable_sort(sup.begin(), sup.end(), [](const SuperTile& x, const SuperTile& y) {
+    const auto longer = [](const SuperTile& x, const SuperTile& y) {
         if (x.K != y.K) return x.K > y.K;
         return x.nm * x.nn > y.nm * y.nn;
-    });
+    };
+    if (!std::is_sorted(sup.begin(), sup.end(), longer)) std::stable_sort(sup.begin(), sup.end(), longer);
     SuperQueues queue(GEMM_XCDS);
-    std::vector<int64_t> work(GEMM_XCDS, 0);
+    for (auto& q : queue) q.reserve(sup.size() / GEMM_XCDS + 1);
+    int64_t work[GEMM_XCDS] = {};
     for (const SuperTile& S : sup) {
-        const int x = (int)(std::min_element(work.begin(), work.end()) - work.begin());
+        const int x = (int)(std::min_element(work, work + GEMM_XCDS) - work);
         queue[x].push_back(S);
         work[x] += (int64_t)S.nm * S.nn * S.K;
     }
@@ -292,21 +294,30 @@ double estimate(const mkor_layer* layers, int stage, const SuperQueues& queue, T
         for (const SuperTile& S : q) tiles += S.nm * S.nn;
         const bool shared = small && tiles > GEMM_XCD_CUS;
         // slots with equal loads, the least loaded first
-        std::map<double, int> busy{{0.0, shared ? 2 * GEMM_XCD_CUS : GEMM_XCD_CUS}};
+        struct { double load; int slots; } busy[2 * GEMM_XCD_CUS + 1] = {{0.0, shared ? 2 * GEMM_XCD_CUS : GEMM_XCD_CUS}};
+        int groups = 1;
         for (const SuperTile& S : q) {
             const bool two = stage == 1 && layers[S.layer].grad_dtype == MKOR_DTYPE_BF16;
             const double cost = (small ? 4.0 : 10.0) +
                                 (small ? (shared ? 0.050 : 0.034) : 0.084) * (two ? 0.72 : 1.0) * S.K;
             for (int left = S.nm * S.nn; left > 0;) {
-                const auto least = busy.begin();
-                const double load = least->first;
-                const int k = std::min(left, least->second);
-                if ((least->second -= k) == 0) busy.erase(least);
-                busy[load + cost] += k;
+                const double load = busy[0].load + cost;
+                const int k = std::min(left, busy[0].slots);
+                if ((busy[0].slots -= k) == 0) std::copy(busy + 1, busy + groups--, busy);
+                int at = groups;
+                while (at > 0 && busy[at - 1].load > load) --at;
+                if (at > 0 && busy[at - 1].load == load) {
+                    busy[at - 1].slots += k;
+                } else {
+                    std::copy_backward(busy + at, busy + groups, busy + groups + 1);
+                    busy[at].load = load;
+                    busy[at].slots = k;
+                    ++groups;
+                }
                 left -= k;
             }
         }
-        worst = std::max(worst, busy.rbegin()->first);
+        worst = std::max(worst, busy[groups - 1].load);
     }
     return worst;
 }
@@ -322,9 +333,11 @@ double estimate(const mkor_layer* layers, int stage, const SuperQueues& queue, T
 // 4096^2 695 and 695 -> 345 and 349, four blocks of a 512-wide encoder 144 and
 // 157 -> 110 and 114; the 72 layers of BERT-Base stay as they were (802 and
 // 761; 914 and 867 on small tiles).
-TilePlan plan_tiles(const mkor_layer* layers, int32_t n, int stage, int family) {
+// queues: the chosen plan's super-tiles.
+TilePlan plan_tiles(const mkor_layer* layers, int32_t n, int stage, int family, SuperQueues& queues) {
     TilePlan best{0, GEMM_SUPER};
     double t = 0.0;
+    queues.clear();
     for (int32_t small = 0; small <= (family == FAM_SPLIT ? 1 : 0); ++small) {
         size_t tiles = 0;
         for (int32_t i = 0; i < n; ++i) {
@@ -332,25 +345,30 @@ TilePlan plan_tiles(const mkor_layer* layers, int32_t n, int stage, int family) 
             const StageGeom g = stage_geom(layers[i], stage, small << (stage - 1));
             tiles += (size_t)ceil_div(g.rows, g.bm) * ceil_div(g.cols, g.bn);
         }
-        if (tiles == 0 || (!small && tiles >= TILES_FULL)) return best;
+        if (tiles == 0) return best;
+        if (!small && tiles >= TILES_FULL) {
+            queues = super_queues(layers, n, stage, family, best);
+            return best;
+        }
         const bool at_once = tiles <= (size_t)GEMM_XCDS * GEMM_XCD_CUS;
         for (int32_t super = at_once ? 256 : GEMM_SUPER; super >= 256; super /= 4) {
             const TilePlan tp{small << (stage - 1), super};
-            const double e = estimate(layers, stage, super_queues(layers, n, stage, family, tp), tp);
+            SuperQueues q = super_queues(layers, n, stage, family, tp);
+            const double e = estimate(layers, stage, q, tp);
             if (t == 0.0 || e < 0.95 * t) {
                 t = e;
                 best = tp;
+                queues.swap(q);
             }
         }
     }
     return best;
 }
 
-// Tile table of one GEMM stage.  Workgroup b runs on XCD b % GEMM_XCDS, so
+// Tile table of a stage's super-tiles.  Workgroup b runs on XCD b % GEMM_XCDS, so
 // position q * GEMM_XCDS + x of the table holds the q-th tile of XCD x;
 // shorter queues are padded with tiles of layer -1.
-std::vector<GemmTile> schedule_tiles(const mkor_layer* layers, int32_t n, int stage, int family, TilePlan tp) {
-    const SuperQueues queue = super_queues(layers, n, stage, family, tp);
+std::vector<GemmTile> schedule_tiles(const SuperQueues& queue) {
     size_t len = 0;
     for (const auto& q : queue) {
         size_t c = 0;
@@ -412,8 +430,6 @@ int32_t mean_rows_per_block(const mkor_layer* layers, int32_t n) {
     return MEAN_ROWS_MIN;
 }
 
-TilePlan tiles_of(const Layout& lo, int stage, int family) { return TilePlan{lo.small, lo.super[family][stage - 1]}; }
-
 }  // namespace
 
 int compute_layout(const mkor_layer* layers, int32_t n, Layout& Lo, bool spare) {
@@ -421,9 +437,10 @@ int compute_layout(const mkor_layer* layers, int32_t n, Layout& Lo, bool spare) 
         for (int stage = 1; stage <= 2; ++stage) {
             // (fp32 MFMA tiles, the layers with a side below 64, keep whole
             // super-tiles: spread, two 3410 x 42 layers took 9 % longer)
-            const TilePlan tp = spare || fam == FAM_FP32 ? TilePlan{0, GEMM_SUPER} : plan_tiles(layers, n, stage, fam);
-            Lo.super[fam][stage - 1] = tp.super;
-            Lo.small |= tp.small;
+            SuperQueues queues;
+            if (spare || fam == FAM_FP32) queues = super_queues(layers, n, stage, fam, TilePlan{0, GEMM_SUPER});
+            else                          Lo.small |= plan_tiles(layers, n, stage, fam, queues).small;
+            Lo.tiles[fam][stage - 1] = schedule_tiles(queues);
         }
     int64_t rowblocks = 0, g1 = 0, gpart = 0, rsb = 0, usum = 0, ncvt = 0, ncvtblk = 0, ntrblk = 0;
     int64_t nqdb = 0;
@@ -470,9 +487,10 @@ int compute_layout(const mkor_layer* layers, int32_t n, Layout& Lo, bool spare) 
     Lo.nmeanpart = mpart;
     Lo.nfactors = 2 * Lo.nsecond;
     Lo.nrowblocks = (int32_t)rowblocks;
-    const size_t t1 = schedule_tiles(layers, n, 1, FAM_FP32, tiles_of(Lo, 1, FAM_FP32)).size(), t2 = schedule_tiles(layers, n, 2, FAM_FP32, tiles_of(Lo, 2, FAM_FP32)).size();
-    const size_t h1 = schedule_tiles(layers, n, 1, FAM_HALF, tiles_of(Lo, 1, FAM_HALF)).size(), h2 = schedule_tiles(layers, n, 2, FAM_HALF, tiles_of(Lo, 2, FAM_HALF)).size();
-    const size_t s1 = schedule_tiles(layers, n, 1, FAM_SPLIT, tiles_of(Lo, 1, FAM_SPLIT)).size(), s2 = schedule_tiles(layers, n, 2, FAM_SPLIT, tiles_of(Lo, 2, FAM_SPLIT)).size();
+    auto ntiles = [&](int fam, int stage) { return Lo.tiles[fam][stage - 1].size(); };
+    const size_t t1 = ntiles(FAM_FP32, 1), t2 = ntiles(FAM_FP32, 2);
+    const size_t h1 = ntiles(FAM_HALF, 1), h2 = ntiles(FAM_HALF, 2);
+    const size_t s1 = ntiles(FAM_SPLIT, 1), s2 = ntiles(FAM_SPLIT, 2);
     if (t1 > INT32_MAX || t2 > INT32_MAX || h1 > INT32_MAX || h2 > INT32_MAX || s1 > INT32_MAX || s2 > INT32_MAX)
         return fail(MKOR_UNSUPPORTED, "layer list too large for one grouped launch");
     Lo.ns1 = (int32_t)s1;
@@ -839,16 +857,10 @@ void build_tables(const mkor_layer* layers, int32_t n, char* base, const Layout&
         gp += ngp;
         dp += ndp;
     }
-    const std::vector<GemmTile> t1 = schedule_tiles(layers, n, 1, FAM_FP32, tiles_of(lo, 1, FAM_FP32)), t2 = schedule_tiles(layers, n, 2, FAM_FP32, tiles_of(lo, 2, FAM_FP32));
-    std::copy(t1.begin(), t1.end(), g1t);
-    std::copy(t2.begin(), t2.end(), g2t);
-    const std::vector<GemmTile> u1 = schedule_tiles(layers, n, 1, FAM_HALF, tiles_of(lo, 1, FAM_HALF)), u2 = schedule_tiles(layers, n, 2, FAM_HALF, tiles_of(lo, 2, FAM_HALF));
-    std::copy(u1.begin(), u1.end(), h1t);
-    std::copy(u2.begin(), u2.end(), h2t);
-    const std::vector<GemmTile> v1 = schedule_tiles(layers, n, 1, FAM_SPLIT, tiles_of(lo, 1, FAM_SPLIT)), v2 = schedule_tiles(layers, n, 2, FAM_SPLIT, tiles_of(lo, 2, FAM_SPLIT));
-    std::copy(v1.begin(), v1.end(), s1t);
-    std::copy(v2.begin(), v2.end(), s2t);
-
+    GemmTile* const out[3][2] = {{g1t, g2t}, {h1t, h2t}, {s1t, s2t}};   // FAM_FP32, FAM_HALF, FAM_SPLIT
+    for (int fam = 0; fam < 3; ++fam)
+        for (int stage = 0; stage < 2; ++stage)
+            std::copy(lo.tiles[fam][stage].begin(), lo.tiles[fam][stage].end(), out[fam][stage]);
 }
 
 int run_stage(const WsView& v, const mkor_params* prm, int32_t stage, hipStream_t s) {
@@ -1046,6 +1058,8 @@ int mkor_plan_create(const mkor_layer* layers, int32_t n, void* d_workspace, siz
     if (plan == nullptr) return fail(MKOR_INVALID_ARG, "out of host memory");
     plan->n = n;
     plan->ws = base;
+    for (auto& family : lo.tiles)
+        for (auto& tiles : family) std::vector<GemmTile>().swap(tiles);   // in `host` now
     plan->lo = lo;
     plan->optbuf.resize(n);
     plan->planned.resize(n);

@@ -50,7 +50,7 @@ struct Layout {
     int32_t nfactors = 0, nrowblocks = 0, ng1 = 0, ng2 = 0, ngpart = 0, ndpart = 0, nrsblocks = 0;
     int32_t nh1 = 0, nh2 = 0;
     int32_t ns1 = 0, ns2 = 0;
-    int32_t super[3][2] = {};   // super-tile extent per GEMM kernel family and stage
+    std::vector<GemmTile> tiles[3][2];   // tile tables per GEMM kernel family and stage
     int32_t small = 0;        // split GEMM stages on SG_BS x SG_BS tiles (bit stage - 1)
     int32_t ncvt = 0, ncvtblk = 0;
     int32_t ntrblk = 0;
