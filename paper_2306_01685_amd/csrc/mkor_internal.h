@@ -110,11 +110,18 @@ constexpr int GRAM = 2 * MAXR * MAXR;
 #endif
 constexpr int SM_GRID = MKOR_SM_GRID;   // workgroups of the SM pass (0: one per row block)
 constexpr int SM_THREADS = 256;
-// Factors of up to 200 MB go through the caches (256 MB of last-level cache): a
-// step of 198 MB of factors 586 -> 570 us, of 93 MB (two 3410 x 42 layers) 2020 ->
-// 1770, of 8 MB (a 1024^2 layer) 109 -> 102.  Larger ones are streamed: 205 MB
-// with a write-back in the call 479 against 485 us, 1.2 GB (an update and its
-// write-back) 716 against 758.
+// Factors of up to RESIDENT_BYTES go through the caches, where the step's GEMMs
+// find them again; larger ones are streamed.  The line is where the 256 MB
+// last-level cache, through which gradients, planes and the intermediate pass
+// between the SM pass and the GEMMs, stops holding them.  Streamed against
+// cached, one step, 512 MB of other data touched between steps:
+//   768-wide encoder blocks   99 MB +5 %, 198 MB +1 %, 297 MB 0
+//   the same with one more input   99 MB +10 %, 198 MB +2 %, 297 MB +1 %
+//   512-wide encoder blocks  132 MB +1 %, 176 MB -1 %, 220 MB -3 %, 264 MB -1 %
+//   2048^2 layers            101 MB +4 %, 134 MB -1 %, 201 MB 0, 235 MB -1 %
+//   3410 x 42 layers          93, 186 and 233 MB +12 %
+// An update and its write-back (768-wide): 99 MB -5 %, 198 MB -2 %, 297 MB -5 %;
+// the same call repeated with nothing between, +15, +22 and +7 %.
 constexpr int64_t RESIDENT_BYTES = 200LL * 1000 * 1000;
 constexpr int SM_ROWS_PER_WAVE = MKOR_SM_RPW;
 constexpr int SM_ROWS = (SM_THREADS / 64) * SM_ROWS_PER_WAVE;
