@@ -61,6 +61,19 @@ def spd(seed, d, spread=0.25):
     return P.astype(np.float32)
 
 
+def fillers(n=128):
+    """Layers that give a plan, with n = 128, the 2048 tiles of 256 x 256 from
+    which it keeps large tiles for every layer of the split."""
+    return H.allocate_layers([(1024, 1024)] * n, "bf16", stats=False)
+
+
+def has_tile(plan, layer, tm, tn) -> bool:
+    """Whether a tile table of the plan (in its workspace) holds tile (tm, tn),
+    tm >= 1, of a layer: which tile size the plan chose."""
+    words = plan.workspace[:plan.workspace.numel() // 8 * 8].view(torch.int64)
+    return bool((words == ((tm << 16 | tn) << 32 | layer)).any())
+
+
 def oparams(p: Params) -> O.Params:
     return O.Params(gamma=p.gamma, zeta=p.zeta, eps=p.eps, norm_kind=p.norm_kind,
                     variant=p.variant, rescale=p.rescale, guard_nonfinite=p.guard_nonfinite)

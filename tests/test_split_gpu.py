@@ -1,5 +1,5 @@
-"""GPU parity of the preconditioning of fp32 factors on the three-way bf16
-split (MKOR_GEMM_SPLIT) against the float64 oracle, and its accuracy beside
+"""GPU parity of the preconditioning of fp32 factors on the 16-bit split
+(MKOR_GEMM_SPLIT) against the float64 oracle, and its accuracy beside
 the fp32 MFMA path (MKOR_GEMM_FP32) on the same inputs.
 
 Bars: relative Frobenius error <= 1e-4 after one step from the same state (as
@@ -97,9 +97,9 @@ def test_split_precondition_only(grad_dtype):
 
 
 def test_split_small_and_large_magnitudes():
-    """The split is exact for operand magnitudes in [2^-110, 3.396e38): factors
-    scaled by 1e-6 and 1e6 (and G with them; every partial product stays a
-    normal fp32 number) keep the fp32-level error."""
+    """The split scales each row by a power of two: factors scaled by 1e-6 and
+    1e6 (and G with them; every partial product stays a normal fp32 number) keep
+    the fp32-level error."""
     for fscale, gscale in ((1e-6, 1e-6), (1e6, 1e3)):
         p = Params(eps=math.inf, rescale=False)
         layers, host = _run("split", "fp32", 90, p, update=False, fscale=fscale, gscale=gscale)
@@ -150,5 +150,5 @@ def test_split_after_sync_and_over_steps():
 def test_split_shape_rule():
     with pytest.raises(MkorError):
         H.make_plan(H.allocate_layers([(64, 96)], "fp32", gemm_path="split"))
-    # AUTO takes the fp32 MFMA path for that shape
+    # AUTO takes that shape
     H.make_plan(H.allocate_layers([(64, 96)], "fp32", gemm_path="auto"))

@@ -1,68 +1,55 @@
-"""The three-way bf16 split behind the fp32-accurate preconditioning on the bf16
-matrix cores (MKOR_GEMM_SPLIT), checked on the CPU with bf16 rounding written
-from its definition (oracle/half.py): x = h + m + l exactly, and the three
-partial products the kernel leaves out stay below 2^-23 |x x'|."""
+"""The products that the split GEMMs form (MKOR_GEMM_SPLIT), checked on the CPU
+against float64: a row's scaled fp16 pairs x = h + l, the three partial
+products kept, the fourth left out, and the one plane of a bf16 gradient."""
 import numpy as np
 
 from oracle.half import round_bf16
+from tests.test_split_scale import pair, split_exp
 
 
-def split3(x32):
-    """h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), each difference taken
-    in fp32 (exact, which the asserts below confirm)."""
-    x = np.asarray(x32, np.float32).astype(np.float64)
-    h = round_bf16(x)
-    r = x - h
-    assert np.array_equal(r.astype(np.float32).astype(np.float64), r)   # exact in fp32
-    m = round_bf16(r)
-    s = r - m
-    assert np.array_equal(s.astype(np.float32).astype(np.float64), s)
-    l = round_bf16(s)
-    return h, m, l, s
+def _row(rng, n, emin, emax):
+    """n values of magnitudes from 2^emin to 2^emax, as one row."""
+    return (rng.choice([-1.0, 1.0], n) * np.ldexp(rng.uniform(1.0, 2.0, n), rng.integers(emin, emax, n))).astype(np.float32)
 
 
-def _samples(rng, n, emin, emax):
-    mant = rng.uniform(1.0, 2.0, n)
-    e = rng.integers(emin, emax, n)
-    sign = rng.choice([-1.0, 1.0], n)
-    return (sign * np.ldexp(mant, e)).astype(np.float32)
-
-
-def test_split_is_exact_over_the_stated_range():
+def test_kept_products_are_exact_in_fp32():
+    """Every factor has 11 significant bits: 22 in a product."""
     rng = np.random.default_rng(0)
-    x = _samples(rng, 200_000, -110, 127)
-    # plus values at the edges of each binade and exact bf16 values
-    x = np.concatenate([x, np.float32([1.0, -1.0, 1.0 + 2.0 ** -23, 2.0 - 2.0 ** -23, 3.0e38, -3.39e38,
-                                       2.0 ** -110, 1.5 * 2.0 ** -110, 0.0])])
-    h, m, l, s = split3(x)
-    assert np.array_equal(l, s)                       # the last piece needs no rounding
-    assert np.array_equal(h + m + l, x.astype(np.float64))
-    ax = np.abs(x.astype(np.float64))
-    assert np.all(np.abs(m) <= 2.0 ** -8 * ax)
-    assert np.all(np.abs(l) <= 2.0 ** -16 * ax)
+    (hx, lx), (hy, ly) = pair(_row(rng, 100_000, -14, 0)), pair(_row(rng, 100_000, -14, 0))
+    for p in (hx * hy, hx * ly, lx * hy):
+        assert np.array_equal(p, p.astype(np.float32).astype(np.float64))
+
+
+def test_dropped_product_is_below_fp32_rounding():
+    """Where no entry falls under fp16's spacing, |l l'| <= 2^-22 |x x'|, and the
+    kept three are within 2^-21 |x x'| of the product."""
+    rng = np.random.default_rng(1)
+    x, y = _row(rng, 100_000, -14, 0), _row(rng, 100_000, -14, 0)
+    (hx, lx), (hy, ly) = pair(x), pair(y)
+    xy = x.astype(np.float64) * y.astype(np.float64)
+    assert np.all(np.abs(lx * ly) <= 2.0 ** -22 * np.abs(xy))
+    assert np.all(np.abs(hx * hy + hx * ly + lx * hy - xy) <= 2.0 ** -21 * np.abs(xy))
+
+
+def test_bf16_gradient_is_one_exact_plane():
+    """Down to 2^-31 of the row's largest entry; below, bits are lost, and below
+    2^-40 the value."""
+    rng = np.random.default_rng(2)
+    g = round_bf16(np.ldexp(rng.uniform(1.0, 2.0, 100_000), rng.integers(-30, 1, 100_000)))
+    s = np.ldexp(g, split_exp(g.max()))
+    assert np.array_equal(s.astype(np.float16).astype(np.float64), s)
+    e = split_exp(1.0)
+    low = round_bf16([2.0 ** -33 * (1 + 2.0 ** -7)])
+    assert np.ldexp(low, e).astype(np.float16).astype(np.float64) != np.ldexp(low, e)
+    assert np.ldexp(round_bf16([2.0 ** -41]), e).astype(np.float16) == 0
 
 
 def test_split_limits():
-    # below 2^-110 the third piece can fall under bf16's subnormal spacing 2^-133
-    x = np.float32(2.0 ** -120 * (1.0 + 2.0 ** -23))
-    h, m, l, s = split3([x])
-    assert not np.array_equal(l, s)
-    # at the bf16 overflow midpoint (2 - 2^-8) 2^127 the first piece becomes infinite
-    assert np.isinf(round_bf16([float(np.float32(3.397e38))])[0])
-    assert np.isfinite(round_bf16([float(np.float32(3.395e38))])[0])
-
-
-def test_dropped_products_are_below_one_fp32_rounding():
-    rng = np.random.default_rng(1)
-    x = _samples(rng, 100_000, -40, 40)
-    y = _samples(rng, 100_000, -40, 40)
-    hx, mx, lx, _ = split3(x)
-    hy, my, ly, _ = split3(y)
-    xy = x.astype(np.float64) * y.astype(np.float64)
-    kept = hx * hy + hx * my + mx * hy + hx * ly + mx * my + lx * hy
-    dropped = mx * ly + lx * my + lx * ly
-    assert np.array_equal(kept + dropped, xy)
-    assert np.all(np.abs(dropped) <= 2.0 ** -23 * np.abs(xy))
-    # with a bf16 operand (G), three products are exact
-    g = round_bf16(y)
-    assert np.array_equal(hx * g + mx * g + lx * g, x.astype(np.float64) * g)
+    """Scales stop at 2^126, so rows of subnormal numbers keep what fp16 holds;
+    rows of the largest finite ones do not overflow; a row with an infinity has
+    the scale 1."""
+    assert split_exp(np.float32(2.0 ** -140)) == 126 and split_exp(np.float32(0.0)) == 0
+    assert split_exp(np.float32(np.inf)) == 0
+    x = np.float32([3.4e38, -3.4e38, 1e30])
+    h, l = pair(x)
+    assert np.all(np.abs(h + l - x.astype(np.float64)) <= 2.0 ** -23 * np.abs(x) + 2.0 ** -39 * 3.4e38)

@@ -1,7 +1,8 @@
 """The scaled fp16 pairs that carry the fp32 operands of the split GEMMs:
-their error bound on the CPU, and on the GPU the 32-row block maxima behind
-the scales wherever they come from (the SM pass, its lazy and rank-r forms,
-the operand preparation of a call without an update, the first GEMM's output).
+their error bounds on the CPU, and on the GPU the row maxima behind the scales
+wherever they come from (the SM pass, its lazy and rank-r forms, the operand
+preparation of a call without an update, the first GEMM's output), ragged
+sizes on both tile sizes, and the one kernel of small layers.
 """
 import math
 
@@ -12,7 +13,7 @@ import torch
 import oracle as O
 from oracle.rank import layer_step_rank
 from paper_2306_01685_amd import Params, harness as H
-from tests.parity import TOL_STEP, check_close, oparams, rel, spd
+from tests.parity import TOL_STEP, check_close, fillers, has_tile, oparams, rel, spd
 
 
 def split_exp(m):
@@ -24,7 +25,7 @@ def split_exp(m):
 
 
 def pair(x):
-    """x (a float32 block) -> its two fp16 planes, scaled back, in float64."""
+    """x (a float32 row) -> its two fp16 planes, scaled back, in float64."""
     e = split_exp(np.abs(x).max())
     xs = np.ldexp(x.astype(np.float64), e)   # exact: a power of two
     h = xs.astype(np.float16)
@@ -35,7 +36,7 @@ def pair(x):
 
 @pytest.mark.parametrize("emin,emax", [(-1, 1), (-14, 0), (-40, 40), (-149, -100), (100, 127)])
 def test_fp16_pair_error(emin, emax):
-    """Within a block with largest entry m: |x - (h + l)| <= 2^-23 |x| + 2^-39 m
+    """Within a row with largest entry m: |x - (h + l)| <= 2^-23 |x| + 2^-39 m
     (l keeps 11 of the remainder's at most 13 bits: half a unit of its last
     place, or half of fp16's spacing 2^-24 under the scale m <= 2^15)."""
     rng = np.random.default_rng(emax + 200)
@@ -45,10 +46,9 @@ def test_fp16_pair_error(emin, emax):
     x = x.astype(np.float64)
     assert np.all(np.abs(x - (h + l)) <= 2.0 ** -23 * np.abs(x) + 2.0 ** -39 * np.abs(x).max())
     assert np.all(np.abs(l) <= 2.0 ** -11 * np.abs(x) + 2.0 ** -39 * np.abs(x).max())   # l l' is left out
-    # 75 % of the mantissas of a well-scaled block are held exactly
+    # 75 % of the mantissas of a well-scaled row are held exactly
     if emax - emin == 2:
         assert np.mean(x == h + l) > 0.7
-
 
 
 @pytest.mark.gpu
@@ -136,7 +136,7 @@ def test_block_scales_of_rank_r_factors_and_switched_layers():
 @pytest.mark.parametrize("shape", [(64, 65), (65, 64), (67, 96), (129, 127), (255, 321), (769, 100), (100, 769), (514, 258)])
 def test_ragged_layers_on_the_split(shape, grad_dtype):
     """AUTO layers of 64 or more that are not multiples of 64: partial slabs,
-    unaligned rows, edges of both tile sizes; precondition alone, then steps
+    unaligned rows, edges of the 128 x 128 tiles; precondition alone, then steps
     with the stabiliser off, on some and on every factor, then a sync."""
     d_in, d_out = shape
     L = H.allocate_layers([shape], grad_dtype)[0]
@@ -173,29 +173,70 @@ def test_ragged_layers_on_the_split(shape, grad_dtype):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("grad_dtype", ["fp32", "bf16"])
+def test_edges_of_large_tiles(grad_dtype):
+    """Ragged and aligned layers among enough others that the plan keeps tiles
+    of 256 x 256 (a bf16 G: 128 x 512), with and without the stabiliser's shift
+    of the diagonal, one and two pending terms."""
+    shapes = [(64, 65), (65, 64), (129, 127), (255, 321), (769, 100), (514, 258), (320, 576), (576, 320), (257, 513)]
+    layers = H.allocate_layers(shapes, grad_dtype)
+    plan = H.make_plan(layers + fillers())
+    assert has_tile(plan, 4, 3, 0) and not has_tile(plan, 4, 6, 0)   # 769 rows: four large tiles, seven small
+    rng = np.random.default_rng(21)
+    st, ins = [], []
+    for i, (L, s) in enumerate(zip(layers, shapes)):
+        Li, Ri = spd(2 * i, s[0]), spd(2 * i + 1, s[1])
+        G = (rng.standard_normal(s) * 1e-3).astype(np.float32)
+        if grad_dtype == "bf16":
+            G = torch.from_numpy(G).bfloat16().float().numpy()
+        ins.append(((rng.standard_normal(s[0]) / math.sqrt(s[0])).astype(np.float32),
+                    (rng.standard_normal(s[1]) / math.sqrt(s[1])).astype(np.float32), G))
+        H.set_factors(L, Li, Ri)
+        H.set_inputs(L, *ins[-1])
+        st.append([Li.astype(np.float64), Ri.astype(np.float64)])
+    plan.precondition(Params(eps=math.inf, rescale=False))
+    torch.cuda.synchronize()
+    for L, (Li, Ri), (_, _, G) in zip(layers, st, ins):
+        check_close(H.get_dW(L), O.precondition(Li, G.astype(np.float64), Ri), 4e-6, G.shape)
+    for t, eps in enumerate((math.inf, 0.0, math.inf)):
+        p = Params(eps=eps)
+        plan.step(p)
+        torch.cuda.synchronize()
+        for i, (L, (a, g, G)) in enumerate(zip(layers, ins)):
+            st[i][0], st[i][1], dW, ost = O.layer_step(st[i][0], st[i][1], a, g, G, oparams(p))
+            check_close(H.get_dW(L), dW, TOL_STEP, shapes[i], t)
+            s = H.get_stats(L)
+            assert s["norm_G"] == pytest.approx(ost.norm_G, rel=1e-6)
+            assert s["norm_dW_hat"] == pytest.approx(ost.norm_dW_hat, rel=1e-5)
+
+
+@pytest.mark.gpu
 def test_tile_sizes_give_the_same_bits():
-    """A layer alone takes small tiles, among many layers large ones: the same
+    """A few layers take small tiles, among many others large ones: the same
     sums in the same order (an output's and ||dW_hat||^2's)."""
     shapes = [(320, 576), (576, 320), (321, 515)]
     rng = np.random.default_rng(3)
     p = Params(eps=math.inf)
 
-    def run(shapes, grad_dtype):
+    def run(grad_dtype, others):
         layers = H.allocate_layers(shapes, grad_dtype, stats=False)
-        plan = H.make_plan(layers)
-        for i, L in enumerate(layers[:3]):
+        plan = H.make_plan(layers + others)
+        # (576 rows: five small tiles, and no more than four of 128 x 512 either way)
+        assert has_tile(plan, 0, 4, 2) == (not others)
+        for i, L in enumerate(layers):
             H.set_factors(L, *fac[i])
             H.set_inputs(L, *ins[i])
         for _ in range(3):
             plan.step(p)
         torch.cuda.synchronize()
-        return [L["dW"].clone() for L in layers[:3]]
+        return [L["dW"].clone() for L in layers]
 
     fac = [(spd(2 * i, s[0]), spd(2 * i + 1, s[1])) for i, s in enumerate(shapes)]
     ins = [((rng.standard_normal(s[0]) / s[0]).astype(np.float32), (rng.standard_normal(s[1]) / s[1]).astype(np.float32),
             torch.from_numpy(rng.standard_normal(s).astype(np.float32)).bfloat16().float().numpy()) for s in shapes]
+    many = fillers()
     for gd in ("fp32", "bf16"):
-        alone, among = run(shapes, gd), run(shapes + [(1024, 1024)] * 60, gd)
+        alone, among = run(gd, []), run(gd, many)
         for x, y in zip(alone, among):
             assert torch.equal(x, y)
 

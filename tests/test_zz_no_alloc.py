@@ -102,6 +102,40 @@ def test_noalloc_matches_plan_two_calls():
     print("worst rel error (vs plan, vs oracle): call 1", w1, "call 2", w2, flush=True)
 
 
+def test_noalloc_list_that_only_just_fits():
+    """63 layers of 257 x 1027 need more than the array on the split's tables and
+    fit on fp32 MFMA: the call gives that path's bits, not the split's."""
+    p = Params(gamma=0.9, zeta=0.5, eps=math.inf)
+    shapes = [(257, 1027)] * 63
+    gen = torch.Generator(device="cuda")
+
+    def build(**kw):
+        gen.manual_seed(5)
+        layers = H.allocate_layers(shapes, "fp32", stats=False, **kw)
+        for L in layers:
+            for k, std in (("a", 0.05), ("g", 1e-3), ("G", 1e-3)):
+                L[k].normal_(0.0, std, generator=gen)
+        return layers
+
+    mine, fp32, auto = build(), build(gemm_path="fp32"), build()
+    B.step_noalloc(mine, p)
+    for layers in (fp32, auto):
+        plan = H.make_plan(layers)
+        plan.step(p)
+        plan.sync_factors()
+        torch.cuda.synchronize()
+        del plan
+    for x, y, z in zip(mine, fp32, auto):
+        assert torch.equal(x["dW"], y["dW"]) and not torch.equal(x["dW"], z["dW"])
+        assert torch.equal(x["Linv"], z["Linv"]) and torch.equal(x["Rinv"], z["Rinv"])
+    for L in (mine[0], mine[-1]):
+        a, g, G = (L[k].cpu().numpy() for k in ("a", "g", "G"))
+        Lo, Ro, dWo, _ = O.layer_step(np.eye(257), np.eye(1027), a, g, G, oparams(p))
+        Lg, Rg = H.get_factors(L)
+        for x, y in ((Lg, Lo), (Rg, Ro), (H.get_dW(L), dWo)):
+            assert rel(x, y) <= TOL_STEP
+
+
 def test_noalloc_stabiliser_and_rejects_oversize():
     # the stabiliser blend (eps = 0 fires on every factor), then a list that
     # needs more than the array holds: rejected on the host, nothing launched
