@@ -414,8 +414,8 @@ int mkor_hybrid_observe(mkor_hybrid_state* state, float loss, int32_t* second_or
  *   - Factors: Linv / Rinv are read, updated and written back within the
  *     call; afterwards they hold the updated factors (nothing is pending).
  *   - Size: a layer list that needs more workspace than
- *     MKOR_NOALLOC_MAX_BYTES, besides descriptors and partial sums (about 2 %
- *     of it), is rejected with MKOR_WORKSPACE_TOO_SMALL before any
+ *     MKOR_NOALLOC_MAX_BYTES, besides descriptors, partial sums and row maxima
+ *     (at most an eighth of it), is rejected with MKOR_WORKSPACE_TOO_SMALL before any
  *     device work; use a plan for it.  A list that only just fits runs on large
  *     tiles, its layers of other sizes than multiples of 64 on MKOR_GEMM_FP32.
  *   - Device and stream: the array of the current device (hipGetDevice) is

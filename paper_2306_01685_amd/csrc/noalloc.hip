@@ -67,7 +67,7 @@ int scratch_address(void** out) {
 // Table bytes travel as kernel arguments, UP_WORDS 4-byte words per launch: as
 // many as fit the 4 KB of a launch's arguments, because a call's time on a
 // small list is its launches (a BERT-Large block: 61 of 1 KB, and 12 others,
-// 574 us; 7 of 3.75 KB, with shorter tables, 520 us).
+// 574 us; 7 of 3.75 KB, with shorter tables, 481 us).
 constexpr int UP_WORDS = 960, UP_THREADS = 320;
 struct UpChunk {
     uint32_t w[UP_WORDS];
